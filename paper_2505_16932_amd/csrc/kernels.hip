@@ -1263,8 +1263,10 @@ __global__ __launch_bounds__((WaveCfg<P, BT>::NT), (BT == 128 ? 2 : 1)) void gem
       banded_decode(local, d.nb, d.nbL, &tm, &tn);
       // the update reads X_t itself (row-major, k along its rows); a matrix past
       // its schedule: no product, the epilogue copies X
-      if (!past)
-        gemm_nt_tile_dl<BT, Acc, W::FN, true>((const uint16_t*)d.Bs, xb_cur(args, d), d.sp, d.Lp, tm * BT,
+      // (the init step's B has a second part)
+      const int parts = past ? 0 : args.init_step ? 2 : 1;
+      for (int h = 0; h < parts; ++h)
+        gemm_nt_tile_dl<BT, Acc, W::FN, true>((const uint16_t*)(h ? d.As : d.Bs), xb_cur(args, d), d.sp, d.Lp, tm * BT,
                                                tn * BT, 0, d.sp, smem, acc);
       epi_update<KIND>(args, d, tm, tn, past, acc, smem);
     } else {
@@ -1406,6 +1408,36 @@ __global__ __launch_bounds__(64) void pw_coef_kernel(KArgs args) {
       int ex = 0;
       if (b != 0.0f) frexpf(2.0f * fabsf(b), &ex);
       d.scal[kScInitQ] = ldexpf(1.0f, 14 - ex);
+    }
+  }
+}
+
+// B = b A - beta I of the init step on the bf16 paths, one row per item, from
+// the FP32 A and in two bf16 parts (Bs, and As, whose A no one reads any more).
+// The cubic cancels at the outlying value (16 - 15 where that is 15 times the
+// rest) and the schedule's slope there is some hundreds, so a relative error of
+// B's top eigenvalue reaches the result 3000 times as large; from the bf16 A,
+// whose rounding is the same for all entries of one mantissa and does not average
+// out, it was 2e-6 to 1.4e-4 (960 x 640: 7.1e-3 against 64 bits).  A pass over A
+// at memory speed.
+__global__ __launch_bounds__(256) void init_b_kernel(KArgs args) {
+  for (int item = blockIdx.x; item < args.total; item += gridDim.x) {
+    const int mi = find_mat(args.offs, args.count, item);
+    CDesc& d = const_desc(args, mi);
+    const int row = item - const_i32(args.offs, mi), sp = d.sp;
+    const float b = d.scal[kScInitB], beta = shift_beta(d, b, 0.0f);
+    if (row == 0 && threadIdx.x == 0) d.scal[kScBeta] = beta;
+    const size_t base = (size_t)row * sp;
+    for (int j = 4 * threadIdx.x; j < sp; j += 4 * blockDim.x) {
+      const f32x4 a = *(const PE_GLOBAL f32x4*)gview(d.Af + base + j);
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = b * a[e] - (j + e == row && row < d.s ? beta : 0.0f);
+      const uint32_t h0 = pack2_bf16(v[0], v[1]), h1 = pack2_bf16(v[2], v[3]);
+      *(PE_GLOBAL u32x2*)(gview_w((uint16_t*)d.Bs) + base + j) = (u32x2){h0, h1};
+      *(PE_GLOBAL u32x2*)(gview_w((uint16_t*)d.As) + base + j) =
+          (u32x2){pack2_bf16(v[0] - __uint_as_float(h0 << 16), v[1] - __uint_as_float(h0 & 0xffff0000u)),
+                  pack2_bf16(v[2] - __uint_as_float(h1 << 16), v[3] - __uint_as_float(h1 & 0xffff0000u))};
     }
   }
 }
@@ -1639,6 +1671,11 @@ hipError_t launch_power(int phase, const KArgs& a, hipStream_t st) {
     const int g = a.count < 1024 ? (a.count > 0 ? a.count : 1) : 1024;
     hipLaunchKernelGGL(pw_coef_kernel, dim3(g), dim3(64), 0, st, a);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_init_b(const KArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(init_b_kernel, dim3(a.total < 4096 ? a.total : 4096), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

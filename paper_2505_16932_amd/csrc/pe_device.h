@@ -20,6 +20,8 @@
 //                           the bA term of B (fp32 path: planes of A, in the
 //                           one of Xb, Xb1 that the step's update will write)
 //   Bs      sp x sp  bf16 (fp32 path: planes)   B - beta I, B = bA + cA^2 (beta: see shift_beta)
+//                           (bf16 paths, spectrum-aware init step: in two bf16
+//                           parts, the second one in As, which is free by then)
 //   Xq, Aq  sp x Lp, sp x sp  e4m3  operand copies for the FP8 steps (256 tile)
 //   part    split-K partial tiles of the Gram-side products
 //   red     per-tile partial sums of squares (fp64) and maxima (fp32) of G

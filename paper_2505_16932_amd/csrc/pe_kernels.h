@@ -32,8 +32,9 @@ __device__ __forceinline__ void st_hint(T* p, T v) {
   else *p = v;
 }
 
-// KIND_UPD0: the first update when X_0 is exactly its bf16 copy (MatDesc::x0b)
-enum Kind : int { KIND_GRAM = 0, KIND_A2 = 1, KIND_UPD = 2, KIND_UPD_LAST = 3, KIND_UPD0 = 4 };
+// KIND_UPD0: the first update when X_0 is exactly its bf16 copy (MatDesc::x0b);
+// KIND_UPDI: the spectrum-aware init step's on the bf16 paths (B in two parts)
+enum Kind : int { KIND_GRAM = 0, KIND_A2 = 1, KIND_UPD = 2, KIND_UPD_LAST = 3, KIND_UPD0 = 4, KIND_UPDI = 5 };
 
 // Descriptor pointers are generic; loads through these global-address-space
 // views compile to global_load (not flat_load), which keeps vmcnt/lgkmcnt apart.

@@ -32,6 +32,7 @@ hipError_t launch_quant(int kind, const KArgs& a, int grid_cap, hipStream_t st);
 hipError_t launch_fast(int prec, int bt, int kind, const KArgs& a, hipStream_t st);
 hipError_t launch_planes(const KArgs& a, hipStream_t st);
 hipError_t launch_power(int phase, const KArgs& a, hipStream_t st);
+hipError_t launch_init_b(const KArgs& a, hipStream_t st);
 hipError_t launch_est(const KArgs& a, int iters, hipStream_t st, const int32_t* offs_a, int total_a,
                       const int32_t* offs_b, int total_b);
 hipError_t launch_mlp_forward(const float* params, const float* feats, int B, float* logits,
@@ -553,7 +554,8 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
     push(PH_PLANES, (q.syrk && prec == kF32) ? (int)(((size_t)q.sp * q.Lp + 16383) / 16384) : 0);
     push_s(PH_RGRAM, (q.syrk && d.gram_split > 1) ? q.syrk : 0);
     push_s(PH_RA2, (q.syrk && d.a2_split > 1) ? q.syrk : 0);
-    push(PH_COMBINE, (q.syrk && learned) ? (int)q.sp : 0);
+    // rows of B formed from a kept A^2 (learned path) or A (init step)
+    push(PH_COMBINE, (q.syrk && (learned || (o->spectral_init > 0 && prec == kBF16))) ? (int)q.sp : 0);
     // quantisation passes: 16384 elements per item (sizes are multiples of 65536)
     push(PH_QX, (q.syrk && q8) ? (int)((size_t)q.sp * q.Lp / 16384) : 0);
     push(PH_QA, (q.syrk && q8) ? (int)((size_t)q.sp * q.sp / 16384) : 0);
@@ -864,6 +866,14 @@ pe_status enqueue_gemm(const pe_plan* p, int t, int kind, hipStream_t st, int fa
   static const int ph_red[3] = {PH_RGRAM, PH_RA2, -1};
   static const char* names[3] = {"gram launch", "a2 launch", "update launch"};
   for (int c = 0; c < kNCls; ++c) {
+    if (t < p->t0 && kind == 1 && cls_prec(c) == kBF16) {
+      if (!p->L.totals[PH_COMBINE][c]) continue;
+      KArgs a = base_args(p);
+      set_phase(p, &a, PH_COMBINE, c);
+      const hipError_t e = launch_init_b(a, st);
+      if (e != hipSuccess) return hip_fail(e, "init step's B");
+      continue;
+    }
     if (!p->L.totals[ph_main[kind]][c]) continue;
     const int bt = cls_bt(c);
     KArgs a = base_args(p);

@@ -285,21 +285,22 @@ __device__ __forceinline__ void wait_stages(int n) {
 }
 
 // The tile's product over k in [k0, k1) (multiples of 64) into the staged LDS
-// tile, one partial tile per group, C::REGION bytes apart.  (__restrict__: the
+// tile, one partial tile per group, C::REGION bytes apart.  P2 (k0 = 0): the
+// product of P + P2, both of k1 columns.  (__restrict__: the
 // alias scopes it leaves on the direct-to-LDS loads keep the compiler from
 // waiting for all of them before every transposing LDS read.)  `inputs` loads
 // what the epilogue reads; it runs once the first stages are on their way, so
 // that all of a tile's first loads share one round trip.
-template <typename C, bool XR, typename F>
+template <typename C, bool XR, bool TWO = false, typename F>
 __device__ __forceinline__ void small_product(const uint16_t* __restrict__ P, const uint16_t* __restrict__ Q, int64_t ld,
                                               int64_t ldQ, size_t plP, size_t plQ, int rp0, int rq0, int k0, int k1,
-                                              char* smem, F&& inputs) {
+                                              char* smem, F&& inputs, const uint16_t* __restrict__ P2 = nullptr) {
   constexpr int BT = C::BT, NS = C::NS, KW = C::KW;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int group = wave / C::WPG, lw = wave % C::WPG;
   const Operands o = {gview(P) + (size_t)rp0 * ld, XR ? gview(Q) + rq0 : gview(Q) + (size_t)rq0 * ldQ,
                       ld, ldQ, plP, plQ};
-  const int nk = (k1 - k0) / C::BK;
+  const int nk = (k1 - k0) / C::BK * (TWO ? 2 : 1);
   f32x4 acc[4][4];
 #pragma unroll
   for (int fm = 0; fm < 4; ++fm)
@@ -309,11 +310,20 @@ __device__ __forceinline__ void small_product(const uint16_t* __restrict__ P, co
   // at the block's barrier, so all run the longest group's count
   const int n = (nk - group + KW - 1) / KW, rounds = C::WPG > 1 ? (nk + KW - 1) / KW : n;
   char* ring = smem + group * C::REGION;
-  auto kofs = [&](int i) { return k0 + (group + KW * i) * C::BK; };
+  auto issue = [&](int i, char* slot) {
+    const int kofs = k0 + (group + KW * i) * C::BK;
+    if (TWO && kofs >= k1) {
+      Operands o2 = o;
+      o2.P = gview(P2) + (size_t)rp0 * ld;
+      small_issue<C, XR>(o2, kofs - k1, slot, lw, lane);
+    } else {
+      small_issue<C, XR>(o, kofs, slot, lw, lane);
+    }
+  };
   // a slot is refilled as soon as it has been read: all slots start full
 #pragma unroll
   for (int i = 0; i < NS; ++i)
-    if (i < n) small_issue<C, XR>(o, kofs(i), ring + i * C::STB, lw, lane);
+    if (i < n) issue(i, ring + i * C::STB);
   inputs();
   const int row0 = C::WPG > 1 ? (lw >> 1) * 64 : 0, col0 = C::WPG > 1 ? (lw & 1) * 64 : 0;
   for (int i = 0; i < rounds; ++i) {
@@ -334,7 +344,7 @@ __device__ __forceinline__ void small_product(const uint16_t* __restrict__ P, co
     wait_lgkm0();  // the slot's reads have returned, after the barrier everyone's
     if constexpr (C::WPG > 1) lds_barrier();
     asm volatile("" ::: "memory");
-    if (i + NS < n) small_issue<C, XR>(o, kofs(i + NS), slot, lw, lane);
+    if (i + NS < n) issue(i + NS, slot);
     if (C::WPG == 1 || i < n) small_mfma<C>(f, acc);
   }
   if constexpr (C::WPG > 1) __syncthreads();  // the tile overlays the group's ring
@@ -629,7 +639,7 @@ __device__ __forceinline__ void load_a(CDesc& d, size_t o, float (&v)[16]) {
 template <int KIND, typename C>
 __global__ __launch_bounds__((C::NT), (C::LDS + kSmallTail <= 80 * 1024 ? 2 : 1)) void small_gemm_kernel(KArgs args) {
   constexpr int BT = C::BT;
-  constexpr bool UPD = KIND == KIND_UPD || KIND == KIND_UPD_LAST || KIND == KIND_UPD0;
+  constexpr bool UPD = KIND == KIND_UPD || KIND == KIND_UPD_LAST || KIND == KIND_UPD0 || KIND == KIND_UPDI;
   __shared__ __attribute__((aligned(16))) char smem[C::LDS + kSmallTail];
   float* cs = (float*)smem;
   float* red = (float*)(smem + C::LDS);
@@ -662,7 +672,7 @@ __global__ __launch_bounds__((C::NT), (C::LDS + kSmallTail <= 80 * 1024 ? 2 : 1)
 #pragma unroll
         for (int p = 0; p < C::NCH; ++p) {
           const size_t o = (size_t)(tm * BT + C::row(p)) * Lp + tn * BT + C::col();
-          if constexpr (KIND == KIND_UPD0) load16(xb_cur(args, d) + o, xr[p]);
+          if (KIND == KIND_UPD0 || (KIND == KIND_UPDI && args.x0b)) load16(xb_cur(args, d) + o, xr[p]);
           else if constexpr (C::PL == 1) load16_halves(xb_at(d, past ? schedule_steps(args, d) : args.t) + o, d.Xl + o, xr[p]);
           else load16(d.Xf + o, xr[p]);
         }
@@ -685,7 +695,8 @@ __global__ __launch_bounds__((C::NT), (C::LDS + kSmallTail <= 80 * 1024 ? 2 : 1)
         inputs();
         tiny_product<true>(args.fast ? d.fb[args.fp_] : (const float*)d.Bs, d.Xf, sp, Lp, tn * BT, 0, past ? 0 : d.sp, d.s, smem);
       } else {
-        small_product<C, true>(Bop, xb_cur(args, d), sp, Lp, sp * sp, sp * Lp, tm * BT, tn * BT, 0, past ? 0 : d.sp, smem, inputs);
+        small_product<C, true, KIND == KIND_UPDI>(Bop, xb_cur(args, d), sp, Lp, sp * sp, sp * Lp, tm * BT, tn * BT, 0,
+                                                  past ? 0 : d.sp, smem, inputs, (const uint16_t*)d.As);
       }
       float amax = 0.0f;
 #pragma unroll
@@ -952,9 +963,9 @@ template <int KIND>
 static void launch_small_k(int prec, int bt, const KArgs& a, hipStream_t st) {
   const bool deep = a.total <= 256;
   if (prec == kTiny) {
-    if constexpr (KIND != KIND_UPD0) launch_small_c<KIND, SmallTile<64, 4, 1, 0>>(a, 256, st);
+    if constexpr (KIND != KIND_UPD0 && KIND != KIND_UPDI) launch_small_c<KIND, SmallTile<64, 4, 1, 0>>(a, 256, st);
   } else if (prec == kF32) {
-    if constexpr (KIND != KIND_UPD0) {
+    if constexpr (KIND != KIND_UPD0 && KIND != KIND_UPDI) {
       if (bt == kTileTiny) {
         if (deep) launch_small_c<KIND, SmallTile<64, 4, 2, 2, 32>>(a, 256, st);
         else launch_small_c<KIND, SmallTile<64, 4, 1, 2, 32>>(a, 512, st);
@@ -977,6 +988,7 @@ hipError_t launch_small_gemm(int prec, int bt, int kind, const KArgs& a, hipStre
   if (kind == KIND_GRAM) launch_small_k<KIND_GRAM>(prec, bt, a, st);
   else if (kind == KIND_A2) launch_small_k<KIND_A2>(prec, bt, a, st);
   else if (a.last) launch_small_k<KIND_UPD_LAST>(prec, bt, a, st);
+  else if (a.init_step && prec == kBF16) launch_small_k<KIND_UPDI>(prec, bt, a, st);
   else if (a.x0b && prec == kBF16) launch_small_k<KIND_UPD0>(prec, bt, a, st);
   else launch_small_k<KIND_UPD>(prec, bt, a, st);
   return hipGetLastError();
@@ -990,6 +1002,7 @@ hipError_t launch_update_tail(KArgs a, hipStream_t st) {
   const int bt = a.total <= 16 ? kTileTiny : kTileSmall, per = 256 / bt;
   a.total *= per * per;
   if (a.last) launch_small_k<KIND_UPD_LAST>(kBF16, bt, a, st);
+  else if (a.init_step) launch_small_k<KIND_UPDI>(kBF16, bt, a, st);
   else if (a.x0b) launch_small_k<KIND_UPD0>(kBF16, bt, a, st);
   else launch_small_k<KIND_UPD>(kBF16, bt, a, st);
   return hipGetLastError();

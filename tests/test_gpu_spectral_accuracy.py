@@ -1,0 +1,84 @@
+"""Accuracy of the spectrum-aware init step on inputs whose outlying value is 15
+times the rest (kappa = z^2 / w^2 of about 240), where its cubic cancels and the
+schedule then has a slope of some hundreds.  bf16 paths: no further from the
+oracle than 1.25 times the same iteration emulated on the CPU with bf16 operands
+(X, A, B rounded once, from 64-bit sums), in which the init step's B is rounded
+once from the unrounded A; both orientations, the 64, 128 and 256 tiles, ragged
+edges, a batch with a short last round of 256 tiles, bf16 and FP32 inputs."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import iteration as OI
+from oracle import spectral_init as SI
+from tests.gpu_util import device_input, oracle_schedule, relf, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pe():
+    import paper_2505_16932_amd as pe
+    pe.lib()
+    return pe
+
+
+def _input(seed, m, n, kappa):
+    k = min(m, n)
+    tail = 1.0 / np.arange(1, k)
+    sig = np.r_[1.0, tail / np.sqrt(kappa * np.sum(tail ** 2))]
+    return synth.usv(synth.rng(seed), m, n, sig).G
+
+
+def _bf16_iteration(vals, abc):
+    import torch
+    m, n = vals.shape
+    X = torch.from_numpy(OI.normalise(vals.T if m > n else vals))
+    low = lambda M: M.to(torch.float32).to(torch.bfloat16).double()
+    s = X.shape[0]
+    eye = torch.eye(s, dtype=torch.float64)
+    H = low(X)
+    A = H @ H.T
+    z = SI.power_lower_bound(A.numpy(), 16)
+    a, b = SI.init_coefficients(z, float(torch.trace(A)) ** 0.5)
+    steps = [(a, b, 0.0)] + [tuple(r) for r in np.asarray(abc).reshape(-1, 3)]
+    for t, (a, b, c) in enumerate(steps):
+        H = low(X)
+        A = H @ H.T
+        Aq = A if t == 0 else low(A)
+        B = b * Aq + (c * (Aq @ Aq) if c else 0.0)
+        beta = float(torch.trace(B)) / s
+        X = (a + beta) * X + low(B - beta * eye) @ H
+    X = X.numpy()
+    return X.T if m > n else X
+
+
+@pytest.mark.parametrize("seed", [1, 2, 3, 4])
+@pytest.mark.parametrize("shape,tile,dtype", [
+    ((256, 700), 1, "bfloat16"), ((960, 640), 1, "bfloat16"), ((960, 640), 2, "float32"), ((512, 1024), 2, "bfloat16"),
+    ((1100, 1024), 0, "float32"), ((1536, 1600), 1, "bfloat16"), ((1536, 1600), 2, "bfloat16")])
+def test_bf16_init_step_rounds_b_once(pe, shape, tile, dtype, seed):
+    import torch
+    G, vals = device_input(_input(8100 + seed, *shape, kappa=240.0), getattr(torch, dtype))
+    abc = oracle_schedule(5)
+    X = pe.polar(G, T=5, abc=abc, compute="bf16", out_dtype=torch.float32, spectral_init=16, tile=tile)
+    torch.cuda.synchronize()
+    ref = SI.spectrum_aware_polar_express(vals, abc, iters=16)
+    e, bar = relf(to_np(X), ref), 1.25 * relf(_bf16_iteration(vals, abc), ref)
+    print(f"[init] {shape} tile {tile} {dtype} seed {seed} relF={e:.3e} bar={bar:.3e}", flush=True)
+    assert e <= bar
+
+
+def test_bf16_init_step_with_a_short_last_round(pe):
+    """18 x 15 update tiles of 256: the last 14 run as smaller ones."""
+    import torch
+    G, vals = device_input(_input(8200, 640, 1200, kappa=240.0), torch.bfloat16)
+    abc = oracle_schedule(5)
+    Xs = pe.polar_batched([G] * 18, T=5, abc=abc, compute="bf16", out_dtype=torch.float32, spectral_init=16, tile=2)
+    torch.cuda.synchronize()
+    ref = SI.spectrum_aware_polar_express(vals, abc, iters=16)
+    bar = 1.25 * relf(_bf16_iteration(vals, abc), ref)
+    for X in (Xs[0], Xs[-1]):
+        e = relf(to_np(X), ref)
+        print(f"[init] batch relF={e:.3e} bar={bar:.3e}", flush=True)
+        assert e <= bar
