@@ -1332,16 +1332,22 @@ __global__ __launch_bounds__((WaveCfg<P, BT>::NT), (BT == 128 ? 2 : 1)) void gem
 // 4096 and 1024 x 1024: 32 launches, 177 us, before; 17 launches now).  The two
 // halves of d.vec take turns as y.
 // ||y|| over [0, sp) (padding is zero), the same bits in every lane
-__device__ __forceinline__ float pw_norm(const float* y, int sp) {
+template <typename F = float>
+__device__ __forceinline__ F pw_norm(const float* y, int sp) {
   const int lane = threadIdx.x & 63;
-  float ss = 0.0f;
+  F ss = 0;
   for (int i = 4 * lane; i < sp; i += 256) {
     const f32x4 v = *(const PE_GLOBAL f32x4*)gview(y + i);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) ss = __builtin_fmaf(v[e], v[e], ss);
+    for (int e = 0; e < 4; ++e) ss = fma((F)v[e], (F)v[e], ss);
   }
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
-  return sqrtf(ss);
+  return sqrt(ss);
+}
+// what pw_matvec_kernel multiplies the previous product by
+__device__ __forceinline__ float pw_inverse(const float* prev, int sp) {
+  const float nrm = pw_norm(prev, sp);
+  return nrm > 0.0f ? 1.0f / nrm : 0.0f;
 }
 
 // one wave per row, four rows per item, from the FP32 A (the fp32 path's own A;
@@ -1369,7 +1375,7 @@ __global__ __launch_bounds__(256) void pw_matvec_kernel(KArgs args) {
         }
       }
     } else {
-      const float nrm = pw_norm(prev, sp), inv = nrm > 0.0f ? 1.0f / nrm : 0.0f;
+      const float inv = pw_inverse(prev, sp);
       for (int j = 4 * lane; j < sp; j += 256) {
         const f32x4 a = *(const PE_GLOBAL f32x4*)gview(row + j), v = *(const PE_GLOBAL f32x4*)gview(prev + j);
 #pragma unroll
@@ -1381,25 +1387,38 @@ __global__ __launch_bounds__(256) void pw_matvec_kernel(KArgs args) {
   }
 }
 
-// after the last power step (est_phase: their number): the init coefficients
+// After the last power step (est_phase: their number): the init coefficients.
+// w^2 = F^2 - z^2 cancels by kappa = z^2 / w^2, so both are formed in FP64 and
+// from the same matrix: z^2 = ||A v|| / ||v|| with the norm that v was left with,
+// and F^2 = tr A or, on the fp32 paths, where the diagonal of A may lack the
+// products of low planes (4e-8 of it, all of one sign), the norm pass's sum times
+// the square of sigma that scaled A.  In FP32 their rounding was 6e-8 kappa
+// of w^2 (2048 x 2304, kappa 1e5: 8.3e-3 of the result against 64 bits).
 __global__ __launch_bounds__(64) void pw_coef_kernel(KArgs args) {
   const int lane = threadIdx.x & 63;
   for (int mi = blockIdx.x; mi < args.count; mi += gridDim.x) {
     CDesc& d = const_desc(args, mi);
     if (d.syrk_nt == 0) continue;
-    const float nrm = pw_norm(d.vec + (size_t)((args.est_phase + 1) & 1) * d.sp, d.sp);
-    // F^2 = tr A from the Gram epilogue's per-tile partials (shift_beta with
-    // b = s, c = 0 returns exactly their fixed-order sum)
-    const float F2 = shift_beta(d, (float)d.s, 0.0f);
+    const float *y = d.vec + (size_t)((args.est_phase + 1) & 1) * d.sp, *prev = d.vec + (size_t)(args.est_phase & 1) * d.sp;
+    const double nv = args.est_phase == 1 ? rsqrtf((float)d.s) * sqrt((double)d.s) : pw_inverse(prev, d.sp) * pw_norm<double>(prev, d.sp);
+    const double z2 = nv > 0.0 ? pw_norm<double>(y, d.sp) / nv : 0.0;
+    double F2 = 0.0;
+    if (d.Xl) {
+      for (int u = lane; u < d.syrk_nt; u += 64) F2 += d.trp[2 * u];
+      F2 = wave_sum(F2);
+    } else {
+      const float sigma = matrix_sigma(args, d);
+      F2 = matrix_square_sum(d) * (sigma * sigma);
+    }
     if (lane == 0) {
       float a = 1.0f, b = 0.0f;
-      const float z = sqrtf(nrm), w2 = F2 - nrm;
-      if (z > 0.0f && w2 > 0.0f) {
-        const float w = sqrtf(w2);
+      const double z = sqrt(z2), w2 = F2 - z2;
+      if (z > 0.0 && w2 > 0.0) {
+        const double w = sqrt(w2);
         if (z > w) {
-          const float den = z * w * (z + w);
-          a = (z * z + z * w + w * w) / den;
-          b = -1.0f / den;
+          const double den = z * w * (z + w);
+          a = (float)((z * z + z * w + w * w) / den);
+          b = (float)(-1.0 / den);
         }
       }
       d.scal[kScInitA] = a;

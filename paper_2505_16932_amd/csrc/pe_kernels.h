@@ -111,6 +111,26 @@ __device__ __forceinline__ float norm_sigma(double fro, int mode) {
   return (float)(mode == 1 ? 1.0 / (fro + 1e-2) : 1.0 / (1.01 * fro + 1e-7));
 }
 
+// sum of a wave's values, the same bits in every lane
+__device__ __forceinline__ double wave_sum(double x) {
+  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
+  return x;
+}
+
+// ||X||_F^2 of the caller's matrix, from the norm pass's partial sums
+__device__ __forceinline__ double matrix_square_sum(CDesc& d) {
+  double acc = 0.0;
+  for (int i = threadIdx.x & 63; i < d.n_prep; i += 64) acc += gview(d.red)[i];
+  return wave_sum(acc);
+}
+
+// sigma of a matrix: from the finalize launch, or (small calls, which save that
+// launch) from the partial sums, which every wave adds up alike
+__device__ __forceinline__ float matrix_sigma(const KArgs& args, CDesc& d) {
+  if (!args.fold_norm) return d.scal[kScScale];
+  return norm_sigma(sqrt(matrix_square_sum(d)), args.norm_mode);
+}
+
 // In the fallback re-run only the matrices whose estimate failed are recomputed.
 template <typename D>
 __device__ __forceinline__ bool skip_matrix(const KArgs& args, D& d) {

@@ -417,16 +417,6 @@ __device__ __forceinline__ void small_gather(const char* smem, int p, float (&x)
   }
 }
 
-// sigma of a matrix: from the finalize launch, or (small calls, which save that
-// launch) from the norm pass's partial sums, which every wave adds up alike
-__device__ __forceinline__ float matrix_sigma(const KArgs& args, CDesc& d) {
-  if (!args.fold_norm) return d.scal[kScScale];
-  double acc = 0.0;
-  for (int i = threadIdx.x & 63; i < d.n_prep; i += 64) acc += gview(d.red)[i];
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  return norm_sigma(sqrt(acc), args.norm_mode);
-}
-
 // The fp32 path's X_0 planes hold G times the power of two below sigma, which
 // rounds nothing; the rest of sigma, in [1, 2), goes into the epilogues of the
 // launches that read them.

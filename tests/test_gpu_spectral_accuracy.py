@@ -4,7 +4,12 @@ schedule then has a slope of some hundreds.  bf16 paths: no further from the
 oracle than 1.25 times the same iteration emulated on the CPU with bf16 operands
 (X, A, B rounded once, from 64-bit sums), in which the init step's B is rounded
 once from the unrounded A; both orientations, the 64, 128 and 256 tiles, ragged
-edges, a batch with a short last round of 256 tiles, bf16 and FP32 inputs."""
+edges, a batch with a short last round of 256 tiles, bf16 and FP32 inputs.
+
+FP32 path: w^2 = F^2 - z^2 cancels by kappa, so that a rounding of z^2 and F^2 to
+FP32 (2^-25 each) moves w^2 by 6e-8 kappa and the init cubic's slope, a ~ 1 / w, by
+half of that; the results stay within 1e-5 + 3e-8 kappa at kappa = 1e6 on the 64 tile
+and on the 128 tile, which it takes by size and by the call's number of tiles."""
 import numpy as np
 import pytest
 
@@ -82,3 +87,17 @@ def test_bf16_init_step_with_a_short_last_round(pe):
         e = relf(to_np(X), ref)
         print(f"[init] batch relF={e:.3e} bar={bar:.3e}", flush=True)
         assert e <= bar
+
+
+@pytest.mark.parametrize("seed", [1, 2])
+@pytest.mark.parametrize("shape,count", [((700, 900), 1), ((700, 900), 40), ((1600, 1700), 1), ((1700, 1600), 1)])
+def test_f32_init_step_keeps_w(pe, shape, count, seed):
+    import torch
+    kappa = 1e6
+    G, vals = device_input(_input(8300 + seed, *shape, kappa=kappa), torch.float32)
+    abc = oracle_schedule(5)
+    X = pe.polar_batched([G] * count, T=5, abc=abc, compute="f32", out_dtype=torch.float32, spectral_init=16)[-1]
+    torch.cuda.synchronize()
+    e = relf(to_np(X), SI.spectrum_aware_polar_express(vals, abc, iters=16))
+    print(f"[init] f32 {shape} x {count} seed {seed} relF={e:.3e}", flush=True)
+    assert e <= 1e-5 + 3e-8 * kappa
