@@ -56,7 +56,9 @@ typedef enum { PE_F32 = 0, PE_BF16 = 1 } pe_dtype;
  *                   accumulation, which is no less accurate than FP32 MFMA
  *                   (matrices with min(m, n) < 16: FP32 operands, FP64 sums;
  *                   FP32 results of T = 6 with min(m, n) > 1024 or T > 6 with
- *                   min(m, n) > 384: FP32 MFMA).
+ *                   min(m, n) > 384, and schedules that grow on [0, 1] past a
+ *                   bound of 8 on X or 128 on B, or in the fast iteration 2048
+ *                   on D: FP32 MFMA).
  *  PE_COMPUTE_BF16: FP32 master iterate; bf16 MFMA operands (X, A, B);
  *                   FP32 accumulation and FP32 epilogues.  Every path
  *                   evaluates the update as (a_t + beta) X + (B - beta I) X,

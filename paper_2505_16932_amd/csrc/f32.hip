@@ -1,5 +1,17 @@
 // The FP32 path on FP32 MFMA (v_mfma_f32_16x16x4_f32, 157 TFLOP/s nominal), for
-// long schedules on matrices of some hundreds of rows and more with an FP32
+// the calls below.
+//
+// Schedules whose polynomials grow on [0, 1].  The planes' scales come from bounds
+// on |p| and |b y + c y^2| there; a spectrum that stays where they are small (a
+// Gaussian 4096 x 4096 has nothing above 0.03) is then held far below its scale,
+// and its low bits and in the end all of it are lost: three steps whose B is
+// bounded by 38 and 1.2e7 were 3e-4 off at s = 1024, (20, -300, 900) and two
+// Newton-Schulz steps gave NaN.  The line lies where the planes are still as
+// close to 64 bits as FP32 MFMA (runtime.hip, planes_fit); schedules for [l, 1]
+// stay below it (X 2, B 16).  All forms of a call: any output, Muon, learned choice,
+// spectrum-aware init, fast iteration.
+//
+// Long schedules on matrices of some hundreds of rows and more with an FP32
 // result.  The small-tile kernels' fp16 planes are two to three times as fast
 // and closer to 64 bits at every size; but each further step multiplies what
 // rounding leaves in the small singular directions, so that two FP32 summations
@@ -101,17 +113,20 @@ template <int KIND>
 __device__ __forceinline__ void f32_epi_syrk(const KArgs& args, CDesc& d, int ti, int tj, const f32x4 (&acc)[4][4], float* red) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const size_t sp = d.sp;
-  float alpha = 1.0f, beta = 0.0f;
+  float alpha = 1.0f, beta = 0.0f, a, b = 0.0f, c = 0.0f;
   if (KIND == KIND_GRAM && args.t == 0) {
     const float sg = d.scal[kScScale];
     alpha = sg * sg;
   }
-  if (KIND == KIND_A2) {
-    beta = shift_beta(d, args.b, args.c);
+  const bool raw = KIND == KIND_A2 && args.raw_a2;  // learned path, step 1: A^2 and its moments
+  if (KIND == KIND_A2 && !raw) {
+    step_coef(args, d, &a, &b, &c);
+    beta = shift_beta(d, b, c);
     if (ti == 0 && tj == 0 && threadIdx.x == 0) d.scal[kScBeta] = beta;
   }
-  float* dst = KIND == KIND_GRAM ? d.Af : (float*)d.Bs;
+  float* dst = KIND == KIND_GRAM ? d.Af : raw ? d.A2f : (float*)d.Bs;
   float trs = 0.0f, frs = 0.0f;
+  float mom[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int fm = 0; fm < 4; ++fm) {
     float ar[4][4];
@@ -132,8 +147,15 @@ __device__ __forceinline__ void f32_epi_syrk(const KArgs& args, CDesc& d, int ti
         if (KIND == KIND_GRAM) {
           v[r] = alpha * x;
           frs = __builtin_fmaf(v[r], v[r], frs);
+        } else if (raw) {
+          const float av = ar[fn][r];
+          v[r] = x;
+          if (ti == tj && i + r == j) mom[0] += av;
+          mom[1] = __builtin_fmaf(av, av, mom[1]);
+          mom[2] = __builtin_fmaf(av, x, mom[2]);
+          mom[3] = __builtin_fmaf(x, x, mom[3]);
         } else {
-          v[r] = __builtin_fmaf(args.c, x, args.b * ar[fn][r]);
+          v[r] = __builtin_fmaf(c, x, b * ar[fn][r]);
           if (ti == tj && i + r == j && j < d.s) v[r] -= beta;
         }
         gview_w(dst)[(size_t)(i + r) * sp + j] = v[r];
@@ -168,14 +190,32 @@ __device__ __forceinline__ void f32_epi_syrk(const KArgs& args, CDesc& d, int ti
       d.trp[2 * tile + 1] = (ti == tj ? 1.0f : 2.0f) * t1;
     }
   }
+  if (raw) {
+    // (an off-diagonal tile also stands for its mirror: weight 2 except on tr A)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      for (int off = 32; off > 0; off >>= 1) mom[k] += __shfl_xor(mom[k], off);
+      if (lane == 0) red[k * 4 + wave] = mom[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+      const float* q = red + threadIdx.x * 4;
+      const float t = ((q[0] + q[1]) + q[2]) + q[3];
+      d.mom[(size_t)tri_index(ti, tj, d.nbs) * 4 + threadIdx.x] = threadIdx.x == 0 || ti == tj ? t : 2.0f * t;
+    }
+  }
 }
 
 // X = alpha ((a + beta) X + acc): the master and the next X^T (the two X^T
 // buffers Xb and Xb1 take turns), or the caller's output on the last step
 template <bool LAST>
-__device__ __forceinline__ void f32_epi_update(const KArgs& args, CDesc& d, int tm, int tn, const f32x4 (&acc)[4][4]) {
+__device__ __forceinline__ void f32_epi_update(const KArgs& args, CDesc& d, int tm, int tn, bool past, const f32x4 (&acc)[4][4]) {
   const size_t Lp = d.Lp, sp = d.sp;
-  const float a = args.a + d.scal[kScBeta], alpha = args.t == 0 ? d.scal[kScScale] : 1.0f;
+  float a, b, c;
+  step_coef(args, d, &a, &b, &c);
+  // (a matrix past its schedule copies X: a = 1)
+  if (!args.fast && !past) a += d.scal[kScBeta];
+  const float alpha = args.t == 0 ? d.scal[kScScale] : 1.0f, keep = 1.0f - args.mlr * args.mwd;
   float* XTn = (float*)((args.t & 1) ? d.Xb : d.Xb1);
 #pragma unroll
   for (int fm = 0; fm < 4; ++fm) {
@@ -199,8 +239,19 @@ __device__ __forceinline__ void f32_epi_update(const KArgs& args, CDesc& d, int 
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           if (i + r < d.s) {
-            const size_t o = d.trans ? (size_t)n * d.ldo + (i + r) : (size_t)(i + r) * d.ldo + n;
-            gview_w((float*)d.Out)[o] = v[r];
+            const size_t row = d.trans ? n : i + r, col = d.trans ? i + r : n;
+            if (d.Out) {
+              const size_t o = row * d.ldo + col;
+              if (d.out_bf16) gview_w((uint16_t*)d.Out)[o] = f2bf(v[r]);
+              else gview_w((float*)d.Out)[o] = v[r];
+            }
+            if (d.W) {
+              const size_t o = row * d.ldw + col;
+              const float w = d.w_bf16 ? bf2f(gview((const uint16_t*)d.W)[o]) : gview((const float*)d.W)[o];
+              const float x = __builtin_fmaf(-args.mlr, v[r], keep * w);
+              if (d.w_bf16) gview_w((uint16_t*)d.W)[o] = f2bf(x);
+              else gview_w((float*)d.W)[o] = x;
+            }
           }
       }
     }
@@ -214,6 +265,9 @@ __global__ __launch_bounds__(kThreads, 2) void f32_gemm_kernel(KArgs args) {
     const int item = xcd_item(slot, args.total);
     const int pos = find_mat(args.offs, args.count, item);
     CDesc& d = const_desc(args, args.ord ? const_i32(args.ord, pos) : pos);
+    if (skip_matrix(args, d)) continue;
+    const bool past = past_schedule(args, d);
+    if (past && KIND != KIND_UPD_LAST) continue;
     const int local = item - const_i32(args.offs, pos);
     f32x4 acc[4][4];
 #pragma unroll
@@ -223,8 +277,9 @@ __global__ __launch_bounds__(kThreads, 2) void f32_gemm_kernel(KArgs args) {
     if constexpr (KIND == KIND_UPD || KIND == KIND_UPD_LAST) {
       int tm, tn;
       banded_decode(local, d.nb, d.nbL, &tm, &tn);
-      f32_product((const float*)d.Bs, (const float*)((args.t & 1) ? d.Xb1 : d.Xb), d.sp, tm * 128, tn * 128, 0, d.sp, smem, acc);
-      f32_epi_update<KIND == KIND_UPD_LAST>(args, d, tm, tn, acc);
+      const float* B = args.fast ? d.fb[args.fp_] : (const float*)d.Bs;
+      if (!past) f32_product(B, (const float*)((args.t & 1) ? d.Xb1 : d.Xb), d.sp, tm * 128, tn * 128, 0, d.sp, smem, acc);
+      f32_epi_update<KIND == KIND_UPD_LAST>(args, d, tm, tn, past, acc);
     } else {
       const int split = KIND == KIND_GRAM ? d.gram_split : d.a2_split;
       const int tile = local / split, ksp = local % split;
@@ -234,8 +289,8 @@ __global__ __launch_bounds__(kThreads, 2) void f32_gemm_kernel(KArgs args) {
       const int K = KIND == KIND_GRAM ? d.Lp : d.sp;
       int k0, k1;
       split_range(K, split, ksp, kBK, &k0, &k1);
-      // a degree-3 step (c = 0) needs no A^2
-      if (KIND == KIND_A2 && args.c == 0.0f) k1 = k0;
+      // a degree-3 step (c = 0 in the fixed schedule) needs no A^2
+      if (KIND == KIND_A2 && !args.sel_coef && args.c == 0.0f) k1 = k0;
       if (k1 > k0) f32_product(Op, Op, K, ti * 128, tj * 128, k0, k1, smem, acc);
       if (split == 1) {
         f32_epi_syrk<KIND>(args, d, ti, tj, acc, (float*)(smem + 4 * kOpB));
@@ -253,10 +308,11 @@ __global__ __launch_bounds__(kThreads, 2) void f32_gemm_kernel(KArgs args) {
 
 template <int KIND>
 __global__ __launch_bounds__(kThreads) void f32_reduce_kernel(KArgs args) {
-  __shared__ float red[8];
+  __shared__ float red[16];
   for (int item = blockIdx.x; item < args.total; item += gridDim.x) {
     const int mi = find_mat(args.offs, args.count, item);
     CDesc& d = const_desc(args, mi);
+    if (skip_matrix(args, d) || past_schedule(args, d)) continue;
     const int tile = item - const_i32(args.offs, mi), split = KIND == KIND_GRAM ? d.gram_split : d.a2_split;
     int ti, tj;
     tri_decode_banded(tile, d.nbs, &ti, &tj);
@@ -271,6 +327,59 @@ __global__ __launch_bounds__(kThreads) void f32_reduce_kernel(KArgs args) {
     f32_epi_syrk<KIND>(args, d, ti, tj, acc, red);
     __syncthreads();
   }
+}
+
+// Products of the fast rectangular iteration (see small_fast_kernel), on FP32
+// buffers: D alternates between two, R is no operand of the product that
+// replaces it.
+template <int KIND>
+__global__ __launch_bounds__(kThreads, 2) void f32_fast_kernel(KArgs args) {
+  __shared__ __attribute__((aligned(16))) char smem[4 * kOpB];
+  for (int slot = blockIdx.x; slot < args.total; slot += gridDim.x) {
+    const int item = xcd_item(slot, args.total);
+    const int pos = find_mat(args.offs, args.count, item);
+    CDesc& d = const_desc(args, pos);
+    int ti, tj;
+    tri_decode_banded(item - const_i32(args.offs, pos), d.nbs, &ti, &tj);
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int fm = 0; fm < 4; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < 4; ++fn) acc[fm][fn] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (KIND == KIND_GRAM) f32_product(d.Xf, d.Xf, d.Lp, ti * 128, tj * 128, 0, d.Lp, smem, acc);
+    else f32_product(d.fb[args.fp_], d.fb[args.fq_], d.sp, ti * 128, tj * 128, 0, d.sp, smem, acc);
+    const size_t sp = d.sp;
+    float ca = args.cacc;
+    if (KIND == KIND_GRAM && args.t == 0) ca *= d.scal[kScScale] * d.scal[kScScale];
+    const float *E1 = args.fe1 >= 0 ? d.fb[args.fe1] : nullptr, *E2 = args.fe2 >= 0 ? d.fb[args.fe2] : nullptr;
+    float* out = d.fb[args.fout];
+#pragma unroll
+    for (int fm = 0; fm < 4; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < 4; ++fn) {
+        const int i = ti * 128 + f32_row(fm), j = tj * 128 + f32_col(fn);
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const size_t o = (size_t)(i + r) * sp + j;
+          float x = ca * acc[fm][fn][r];
+          if (E1) x = __builtin_fmaf(args.c1, gview(E1)[o], x);
+          if (E2) x = __builtin_fmaf(args.c2, gview(E2)[o], x);
+          if (i + r == j && j < d.s) x += args.cdiag;
+          v[r] = x;
+          gview_w(out)[o] = x;
+        }
+        if (ti != tj) *(PE_GLOBAL f32x4*)gview_w(out + (size_t)j * sp + i) = (f32x4){v[0], v[1], v[2], v[3]};
+      }
+    __syncthreads();  // the stages are free for the next tile
+  }
+}
+
+hipError_t launch_f32_fast(int kind, const KArgs& a, hipStream_t st) {
+  if (a.total <= 0) return hipSuccess;
+  auto k = kind == KIND_GRAM ? f32_fast_kernel<KIND_GRAM> : f32_fast_kernel<KIND_A2>;
+  hipLaunchKernelGGL(k, dim3(a.total < 512 ? a.total : 512), dim3(kThreads), 0, st, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_f32_gemm(int kind, const KArgs& a, hipStream_t st) {

@@ -422,7 +422,7 @@ hipError_t launch_select(const KArgs& a, hipStream_t st) {
 
 hipError_t launch_combine(int prec, const KArgs& a, hipStream_t st) {
   const int g = a.total < 4096 ? (a.total > 0 ? a.total : 1) : 4096;
-  if (prec == kTiny) hipLaunchKernelGGL(combine_kernel<kTiny>, dim3(g), dim3(256), 0, st, a);
+  if (prec == kTiny || prec == kF32M) hipLaunchKernelGGL(combine_kernel<kTiny>, dim3(g), dim3(256), 0, st, a);
   else if (prec == kF32) hipLaunchKernelGGL(combine_kernel<kF32>, dim3(g), dim3(256), 0, st, a);
   else hipLaunchKernelGGL(combine_kernel<kBF16>, dim3(g), dim3(256), 0, st, a);
   return hipGetLastError();

@@ -55,7 +55,7 @@ constexpr int kThreads = 256;   // threads per block (4 wave64)
 constexpr int kMaxSteps = 64;
 
 // kTiny: the fp32 path of matrices with fewer than 16 rows, without planes;
-// kF32M: FP32 MFMA (f32.hip), X^T in Xb / Xb1 and fp32 B
+// kF32M: FP32 MFMA (f32.hip), X^T in Xb / Xb1, fp32 B and fb
 enum Prec : int32_t { kF32 = 0, kBF16 = 1, kFP8 = 2, kTiny = 3, kF32M = 4 };
 
 // scal[] slots

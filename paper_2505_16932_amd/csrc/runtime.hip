@@ -50,6 +50,7 @@ hipError_t launch_small_gemm(int prec, int bt, int kind, const KArgs& a, hipStre
 hipError_t launch_resident(int bucket, const KArgs& a, const ResSchedule& s, hipStream_t st);
 hipError_t launch_f32_gemm(int kind, const KArgs& a, hipStream_t st);
 hipError_t launch_f32_reduce(int kind, const KArgs& a, hipStream_t st);
+hipError_t launch_f32_fast(int kind, const KArgs& a, hipStream_t st);
 hipError_t launch_small_reduce(int prec, int bt, int kind, const KArgs& a, hipStream_t st);
 }  // namespace pe
 
@@ -201,15 +202,170 @@ std::string shape_class(int prec, int64_t s, int64_t L) {
   return buf;
 }
 
+// Largest bounds with which operands stay in planes (planes_fit)
+constexpr double kFitX = 8.0, kFitB = 128.0, kFitD = 2048.0;
+
+// Largest power of two q with q * bound <= 2^14 (a quarter of the fp16 range).
+float plane_scale(double bound) {
+  if (!(bound > 1e-30)) bound = 1e-30;
+  if (!(bound < 1e30)) bound = 1e30;
+  return (float)std::ldexp(1.0, 14 - (int)std::ceil(std::log2(bound)));
+}
+
+// Bounds on the singular values of the fp32 path's operands per kernel step.
+// X_0 = G / (1.01 ||G||_F + ..) has none above 1; a step with p(x) = a x + b x^3
+// + c x^5 takes a bound u to max |p| on [0, u] (the quarter of the range that
+// plane_scale leaves covers the rounding of the iterate), A has norm u^2 and
+// B - beta I twice max |b y + c y^2| at most.  The learned path takes the
+// largest bound over the classes.  The spectrum-aware step's cubic is chosen on
+// the device, which also chooses the scale of its B (kScInitQ); it maps the
+// spectrum to [0, 1] where its power method has converged.
+struct PlaneBounds {
+  std::vector<double> x, a, b;
+};
+PlaneBounds plane_bounds(const std::vector<std::vector<double>>& tables, int T, int t0) {
+  const int n = T + t0;
+  PlaneBounds r;
+  r.x.assign(n + 1, 0.0);
+  r.a.assign(n, 0.0);
+  r.b.assign(n, 0.0);
+  for (const auto& abc : tables) {
+    double u = 1.0;
+    for (int t = 0; t < n; ++t) {
+      r.x[t] = std::max(r.x[t], u);
+      r.a[t] = std::max(r.a[t], u * u);
+      if (t >= t0) {
+        const double* k = &abc[3 * (t - t0)];
+        double un = 0.0, bn = 0.0;
+        auto at = [&](double y) {  // y = x^2 in [0, u^2]
+          if (!(y > 0.0) || y > u * u) return;
+          const double h = y * (k[1] + k[2] * y);
+          un = std::max(un, std::sqrt(y) * std::fabs(k[0] + h));
+          bn = std::max(bn, std::fabs(h));
+        };
+        // the ends and the extrema of p (a + 3 b y + 5 c y^2 = 0) and of b y + c y^2
+        at(u * u);
+        at(-k[1] / (2.0 * k[2]));
+        const double disc = 9.0 * k[1] * k[1] - 20.0 * k[0] * k[2];
+        if (disc >= 0.0) {
+          at((-3.0 * k[1] + std::sqrt(disc)) / (10.0 * k[2]));
+          at((-3.0 * k[1] - std::sqrt(disc)) / (10.0 * k[2]));
+        }
+        if (k[2] == 0.0) at(-k[0] / (3.0 * k[1]));
+        r.b[t] = std::max(r.b[t], 2.0 * bn);
+        u = std::min(std::max(un, 1e-20), 1e20);
+      }
+    }
+    r.x[n] = std::max(r.x[n], u);
+  }
+  return r;
+}
+
+// The products of the fast rectangular iteration in order (see
+// small_fast_kernel), in segments of `restart` steps:
+//   product(seg, kind, fp, fq, e1, c1, e2, c2, cacc, out, cdiag)
+//   update(seg, last, q, D)
+template <typename P, typename U>
+pe_status fast_walk(const float* abc, int T, int restart, float eps, P&& product, U&& update) {
+  pe_status s;
+  int seg = 0;
+  for (int t0 = 0; t0 < T; t0 += restart, ++seg) {
+    const int k = std::min(restart, T - t0);
+    int dcur = kFbD0;
+    // Y = X X^T (of the normalised X_0 in the first segment, plus eps I)
+    if ((s = product(seg, 0, -1, -1, kFbNone, 0.f, kFbNone, 0.f, 1.f, kFbR, seg == 0 ? eps : 0.f)) != PE_OK) return s;
+    float q = 1.0f;
+    for (int j = 0; j < k; ++j) {
+      const float a = abc[3 * (t0 + j)], b = abc[3 * (t0 + j) + 1], cc = abc[3 * (t0 + j) + 2];
+      // B_t = b R + c R^2 (into D directly on the segment's first step, D_1 = B_1)
+      const int bdst = j == 0 ? dcur : kFbB;
+      if ((s = product(seg, 1, kFbR, kFbR, kFbR, b, kFbNone, 0.f, cc, bdst, 0.f)) != PE_OK) return s;
+      if (j > 0) {
+        const int dn = dcur == kFbD0 ? kFbD1 : kFbD0;
+        if ((s = product(seg, 1, dcur, kFbB, dcur, a, kFbB, q, 1.f, dn, 0.f)) != PE_OK) return s;
+        dcur = dn;
+      }
+      if (j + 1 < k) {
+        if ((s = product(seg, 1, kFbR, bdst, kFbNone, 0.f, kFbNone, 0.f, 1.f, kFbP, 0.f)) != PE_OK) return s;
+        if ((s = product(seg, 1, kFbP, bdst, kFbR, a * a, kFbP, 2.f * a, 1.f, kFbR, 0.f)) != PE_OK) return s;
+      }
+      q *= a;
+    }
+    if ((s = update(seg, t0 + k >= T, q, dcur)) != PE_OK) return s;
+  }
+  return PE_OK;
+}
+
+// Bounds on its operands in the same order, one per product and update (the
+// next X), from the recursions on scalars sampled over each segment's spectrum
+// [0, u^2]; grew: whether one is past the planes' reach (see planes_fit).
+std::vector<double> fast_bounds(const float* abc, int T, int restart, float eps, bool* grew) {
+  constexpr int kSamples = 256;
+  typedef std::vector<double> Vec;
+  Vec y(kSamples), val[5], out;
+  for (auto& v : val) v.assign(kSamples, 0.0);
+  double u = 1.0;
+  *grew = false;
+  auto product = [&](int, int kind, int fp_, int fq_, int fe1, float c1, int fe2, float c2, float cacc, int fout,
+                     float cdiag) {
+    if (kind == 0)
+      for (int i = 0; i < kSamples; ++i) y[i] = u * u * (i + 1) / kSamples;
+    Vec v(kSamples);
+    double m = 0.0;
+    for (int i = 0; i < kSamples; ++i) {
+      v[i] = cacc * (kind == 0 ? y[i] : val[fp_][i] * val[fq_][i]) + cdiag;
+      if (fe1 >= 0) v[i] += c1 * val[fe1][i];
+      if (fe2 >= 0) v[i] += c2 * val[fe2][i];
+      m = std::max(m, std::fabs(v[i]));
+    }
+    val[fout] = v;
+    out.push_back(m);
+    *grew = *grew || !(m <= (fout == kFbD0 || fout == kFbD1 ? kFitD : kFitB));
+    return PE_OK;
+  };
+  auto update = [&](int, bool last, float q, int dcur) {
+    double un = 1e-20;
+    for (int i = 0; i < kSamples; ++i) un = std::max(un, std::sqrt(y[i]) * std::fabs(q + val[dcur][i]));
+    u = std::min(un, 1e20);
+    out.push_back(u);
+    *grew = *grew || (!last && !(u <= kFitX));
+    return PE_OK;
+  };
+  (void)fast_walk(abc, T, restart, eps, product, update);
+  return out;
+}
+
+// Whether the schedule keeps within the operand planes' reach.  An operand is
+// held to 2^-39 of its bound, so what matters is how far the bound can lie above
+// the values: measured with a first step (k, 0, 0) and Newton-Schulz steps on
+// Gaussian inputs, planes against FP32 MFMA: X bounded by 4, B by 152: 4.6e-8 and
+// 4.5e-8 (s = 4096); X 2, B 737: 6.0e-8 and 4.7e-8; X 8, B 2.9e3: 1.6e-7 and
+// 5.0e-8; the fast iteration with D bounded by 2.6e3 and R, B, P by 441 3.8e-8
+// and 3.9e-8, by 1.2e4 and 1.5e3 8.2e-8 and 4.6e-8.  Schedules for [l, 1] have
+// X 2, B 16, and in segments of three steps D 130.
+bool planes_fit(const pe_opts* o) {
+  std::vector<float> abc(o->abc, o->abc + 3 * o->T);
+  if (o->fast_restart > 0) {
+    bool grew = false;
+    fast_bounds(abc.data(), o->T, o->fast_restart, o->fast_eps, &grew);
+    return !grew;
+  }
+  const PlaneBounds r = plane_bounds({std::vector<double>(abc.begin(), abc.end())}, o->T, 0);
+  for (int t = 0; t < o->T; ++t)
+    if (!(r.x[t] <= kFitX) || !(r.b[t] <= kFitB)) return false;
+  return true;
+}
+
 // Precision of one matrix: FP32 on the FP32 path; on the bf16/FP8 paths FP32
 // as well when the smaller side is below kTinyS, where a handful of singular
 // values leave bf16 rounding errors nothing to average over (relative errors
 // up to ~1e-1 at s = 2-8 on Gaussian inputs) and the products cost nothing.
 constexpr int64_t kTinyS = 16;
-int prec_for(const pe_opts* o, const pe_matrix& m) {
+int prec_for(const pe_opts* o, const pe_matrix& m, bool fit) {
   const int64_t s = std::min(m.m, m.n);
   if (s < kTinyS) return kTiny;
   if (o->compute != PE_COMPUTE_F32) return kBF16;
+  if (!fit) return kF32M;
   // FP32 results of long schedules stay with FP32 MFMA's summation order (see
   // f32.hip for where the lines lie); a bf16 result or a weight step hides the
   // difference, and the fast, learned and spectrum-aware forms have their own
@@ -326,6 +482,7 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
   std::vector<Shape> sh;
   int64_t syrk_total[kNCls] = {}, tiles128 = 0;
   int fits = 0, present = 0;
+  const bool fit = o->compute != PE_COMPUTE_F32 || planes_fit(o);
   int64_t prep_tiles = 0, most_prep = 0;
   bool f32m = false, small_only = true;
   for (int i = 0; i < count; ++i) {
@@ -336,7 +493,7 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
     if (m.m > 0 && m.n > 0) {
       q.s = std::min(m.m, m.n);
       q.L = std::max(m.m, m.n);
-      q.prec = prec_for(o, m);
+      q.prec = prec_for(o, m, fit);
       q.bt = q.sbt = tile_for(o, q.prec, q.s, q.L, batch_regime, upd256);
       // (e4m3 steps convert their operands on the 128 tile while staging them)
       q.family = q.prec == kF32 || q.prec == kTiny || (q.prec == kBF16 && q.bt == kTileSmall && !fp8);
@@ -506,10 +663,10 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
       }
       if (o->fast_restart > 0)
         // both D share their fp32 values, which a product replaces in place; a
-        // kTiny product reads them as operands, and has no planes
+        // kTiny or kF32M product reads them as operands, and has no planes
         for (int k = 0; k < 5; ++k) {
-          d.fb[k] = k == kFbD1 && prec != kTiny ? d.fb[kFbD0] : (float*)take(A * 4);
-          d.fbp[k] = prec != kTiny && k != kFbP ? (uint16_t*)take(A * 4) : nullptr;
+          d.fb[k] = k == kFbD1 && prec == kF32 ? d.fb[kFbD0] : (float*)take(A * 4);
+          d.fbp[k] = prec == kF32 && k != kFbP ? (uint16_t*)take(A * 4) : nullptr;
         }
       if (o->spectral_init > 0 && !learned) d.vec = (float*)take(((size_t)2 * q.sp + q.Lp) * 4);
       if (learned) {
@@ -667,6 +824,7 @@ struct pe_plan {
   std::vector<float> abc;
   // fp32 path: scales of the operand planes of X_t, A_t and B_t per kernel step
   std::vector<float> sx, sa, sb;
+  std::vector<float> sfast; // fast iteration: of each product's result, and of the next X after a segment
   bool learned = false;
   const float* mlp = nullptr;
   int force_class = -1;
@@ -732,63 +890,6 @@ pe_status upload(pe_plan* p, char* ws, const std::vector<std::vector<double>>& t
   p->d_coef = (float*)(ws + p->L.coef_off);
   p->d_steps = (int32_t*)(p->d_coef + nt);
   return put_words(p->d_coef, tab.data(), tab.size() * 4, st);
-}
-
-// Largest power of two q with q * bound <= 2^14 (a quarter of the fp16 range).
-float plane_scale(double bound) {
-  if (!(bound > 1e-30)) bound = 1e-30;
-  if (!(bound < 1e30)) bound = 1e30;
-  return (float)std::ldexp(1.0, 14 - (int)std::ceil(std::log2(bound)));
-}
-
-// Scales of the fp32 path's operand planes from bounds on the singular values.
-// X_0 = G / (1.01 ||G||_F + ..) has none above 1; a step with p(x) = a x + b x^3
-// + c x^5 takes a bound u to max |p| on [0, u] (the quarter of the range that
-// plane_scale leaves covers the rounding of the iterate), A has norm u^2 and
-// B - beta I twice max |b y + c y^2| at most.  The learned path takes the
-// largest bound over the classes.  The spectrum-aware step's cubic is chosen on
-// the device, which also chooses the scale of its B (kScInitQ); it maps the
-// spectrum to [0, 1] where its power method has converged.
-void plane_bounds(pe_plan* p, const std::vector<std::vector<double>>& tables) {
-  const int n = p->T + p->t0;
-  std::vector<double> ux(n + 1, 0.0), ua(n, 0.0), ub(n, 0.0);
-  for (const auto& abc : tables) {
-    double u = 1.0;
-    for (int t = 0; t < n; ++t) {
-      ux[t] = std::max(ux[t], u);
-      ua[t] = std::max(ua[t], u * u);
-      if (t >= p->t0) {
-        const double* k = &abc[3 * (t - p->t0)];
-        double un = 0.0, bn = 0.0;
-        auto at = [&](double y) {  // y = x^2 in [0, u^2]
-          if (!(y > 0.0) || y > u * u) return;
-          const double h = y * (k[1] + k[2] * y);
-          un = std::max(un, std::sqrt(y) * std::fabs(k[0] + h));
-          bn = std::max(bn, std::fabs(h));
-        };
-        // the ends and the extrema of p (a + 3 b y + 5 c y^2 = 0) and of b y + c y^2
-        at(u * u);
-        at(-k[1] / (2.0 * k[2]));
-        const double disc = 9.0 * k[1] * k[1] - 20.0 * k[0] * k[2];
-        if (disc >= 0.0) {
-          at((-3.0 * k[1] + std::sqrt(disc)) / (10.0 * k[2]));
-          at((-3.0 * k[1] - std::sqrt(disc)) / (10.0 * k[2]));
-        }
-        if (k[2] == 0.0) at(-k[0] / (3.0 * k[1]));
-        ub[t] = std::max(ub[t], 2.0 * bn);
-        u = std::min(std::max(un, 1e-20), 1e20);
-      }
-    }
-    ux[n] = std::max(ux[n], u);
-  }
-  p->sx.resize(n + 1);
-  p->sa.resize(n);
-  p->sb.resize(n);
-  for (int t = 0; t <= n; ++t) p->sx[t] = plane_scale(ux[t]);
-  for (int t = 0; t < n; ++t) {
-    p->sa[t] = plane_scale(ua[t]);
-    p->sb[t] = t < p->t0 ? 1.0f : plane_scale(ub[t]);
-  }
 }
 
 KArgs base_args(const pe_plan* p) {
@@ -933,37 +1034,16 @@ pe_status enqueue_select(const pe_plan* p, hipStream_t st) {
 
 // Algorithm 4 in segments of fast_restart steps (FP32 classes only): per
 // segment the Gram matrix, then per step B_t, D_t and (but for the last step)
-// R_{t+1}, and the update X <- q X + D X; see small_fast_kernel.  The operand
-// planes' scales come from the same recursions on scalars, sampled over the
-// segment's spectrum [0, u^2].
+// R_{t+1}, and the update X <- q X + D X; see small_fast_kernel.
 pe_status enqueue_fast(const pe_plan* p, hipStream_t st) {
   pe_status s = enqueue_norm(p, st, 0);
   if (s != PE_OK) return s;
   hipError_t e;
-  constexpr int kSamples = 256;
-  typedef std::vector<double> Vec;
-  Vec y(kSamples), val[5];
-  for (auto& v : val) v.assign(kSamples, 0.0);
-  float scale[5] = {};
-  double u = 1.0;
-  auto scale_of = [&](int k) {
-    double m = 0.0;
-    for (double x : val[k]) m = std::max(m, std::fabs(x));
-    return plane_scale(m);
-  };
-  // kind 0: Gram of X, 1: symmetric product of two fb buffers; val[fout] holds
-  // the product's values on the samples
-  auto product = [&](int kind, int fp_, int fq_, int fe1, float c1, int fe2, float c2, float cacc,
-                     int fout, float cdiag, int seg) -> pe_status {
-    Vec out(kSamples);
-    for (int i = 0; i < kSamples; ++i) {
-      double x = cacc * (kind == 0 ? y[i] : val[fp_][i] * val[fq_][i]) + cdiag;
-      if (fe1 >= 0) x += c1 * val[fe1][i];
-      if (fe2 >= 0) x += c2 * val[fe2][i];
-      out[i] = x;
-    }
-    val[fout] = out;
-    const float sx = plane_scale(u);
+  const float* next = p->sfast.data();
+  float sx = p->sx[0], scale[5] = {};
+  // kind 0: Gram of X, 1: symmetric product of two fb buffers
+  auto product = [&](int seg, int kind, int fp_, int fq_, int fe1, float c1, int fe2, float c2, float cacc, int fout,
+                     float cdiag) -> pe_status {
     KArgs a = base_args(p);
     a.t = seg;
     a.fast = 1;
@@ -977,62 +1057,36 @@ pe_status enqueue_fast(const pe_plan* p, hipStream_t st) {
     a.fout = fout;
     a.cdiag = cdiag;
     const float deq = kind == 0 ? 1.0f / sx / sx : 1.0f / scale[fp_] / scale[fq_];
-    a.oscale = scale_of(fout);
+    a.oscale = scale[fout] = *next++;
     for (int c = 0; c < kNCls; ++c) {
       if (!p->L.totals[PH_FSYRK][c]) continue;
       set_phase(p, &a, PH_FSYRK, c);
       a.deq = cls_prec(c) == kF32 ? deq : 1.0f;
-      if ((e = launch_fast(cls_prec(c), cls_bt(c), kind, a, st)) != hipSuccess) return hip_fail(e, "fast product");
+      e = cls_prec(c) == kF32M ? launch_f32_fast(kind, a, st) : launch_fast(cls_prec(c), cls_bt(c), kind, a, st);
+      if (e != hipSuccess) return hip_fail(e, "fast product");
     }
-    scale[fout] = a.oscale;
     return PE_OK;
   };
-  int seg = 0;
-  for (int t0 = 0; t0 < p->T; t0 += p->fast_restart, ++seg) {
-    const int k = std::min(p->fast_restart, p->T - t0);
-    int dcur = kFbD0;
-    for (int i = 0; i < kSamples; ++i) y[i] = u * u * (i + 1) / kSamples;
-    // Y = X X^T (of the normalised X_0 in the first segment, plus eps I)
-    if ((s = product(0, -1, -1, kFbNone, 0.f, kFbNone, 0.f, 1.f, kFbR, seg == 0 ? p->fast_eps : 0.f, seg)) != PE_OK)
-      return s;
-    float q = 1.0f;
-    for (int j = 0; j < k; ++j) {
-      const float a = p->abc[3 * (t0 + j)], b = p->abc[3 * (t0 + j) + 1], cc = p->abc[3 * (t0 + j) + 2];
-      // B_t = b R + c R^2 (into D directly on the segment's first step, D_1 = B_1)
-      const int bdst = j == 0 ? dcur : kFbB;
-      if ((s = product(1, kFbR, kFbR, kFbR, b, kFbNone, 0.f, cc, bdst, 0.f, seg)) != PE_OK) return s;
-      if (j > 0) {
-        const int dn = dcur == kFbD0 ? kFbD1 : kFbD0;
-        if ((s = product(1, dcur, kFbB, dcur, a, kFbB, q, 1.f, dn, 0.f, seg)) != PE_OK) return s;
-        dcur = dn;
-      }
-      if (j + 1 < k) {
-        if ((s = product(1, kFbR, bdst, kFbNone, 0.f, kFbNone, 0.f, 1.f, kFbP, 0.f, seg)) != PE_OK) return s;
-        if ((s = product(1, kFbP, bdst, kFbR, a * a, kFbP, 2.f * a, 1.f, kFbR, 0.f, seg)) != PE_OK) return s;
-      }
-      q *= a;
-    }
-    // X <- q X + D X
-    const float sx = plane_scale(u);
-    double un = 1e-20;
-    for (int i = 0; i < kSamples; ++i) un = std::max(un, std::sqrt(y[i]) * std::fabs(q + val[dcur][i]));
-    u = std::min(un, 1e20);
+  // X <- q X + D X
+  auto update = [&](int seg, bool last, float q, int dcur) -> pe_status {
     KArgs a = base_args(p);
     a.t = seg;
-    a.last = t0 + k >= p->T;
+    a.last = last;
     a.a = q;
     a.b = a.c = 0.0f;
     a.fast = 1;
     a.fp_ = dcur;
     a.deq = 1.0f / scale[dcur] / sx;
-    a.oscale = plane_scale(u);
+    a.oscale = sx = *next++;
     for (int c = 0; c < kNCls; ++c) {
       if (!p->L.totals[PH_UPD][c]) continue;
       set_phase(p, &a, PH_UPD, c);
-      if ((e = launch_small_gemm(cls_prec(c), cls_bt(c), 2, a, st)) != hipSuccess) return hip_fail(e, "fast update");
+      e = cls_prec(c) == kF32M ? launch_f32_gemm(2, a, st) : launch_small_gemm(cls_prec(c), cls_bt(c), 2, a, st);
+      if (e != hipSuccess) return hip_fail(e, "fast update");
     }
-  }
-  return PE_OK;
+    return PE_OK;
+  };
+  return fast_walk(p->abc.data(), p->T, p->fast_restart, p->fast_eps, product, update);
 }
 
 // power method on each matrix's step-1 Gram matrix and the init coefficients
@@ -1125,7 +1179,14 @@ pe_status plan_init(pe_plan* p, int count, const pe_matrix* mats, const pe_opts*
   std::vector<std::vector<double>> tables;
   s = class_tables(p, &tables);
   if (s != PE_OK) return s;
-  plane_bounds(p, tables);
+  const PlaneBounds bounds = plane_bounds(tables, p->T, p->t0);
+  for (double v : bounds.x) p->sx.push_back(plane_scale(v));
+  for (double v : bounds.a) p->sa.push_back(plane_scale(v));
+  for (int t = 0; t < p->T + p->t0; ++t) p->sb.push_back(t < p->t0 ? 1.0f : plane_scale(bounds.b[t]));
+  if (p->fast_restart > 0) {
+    bool grew;
+    for (double v : fast_bounds(p->abc.data(), p->T, p->fast_restart, p->fast_eps, &grew)) p->sfast.push_back(plane_scale(v));
+  }
   return upload(p, (char*)ws, tables, st);
 }
 
