@@ -298,9 +298,10 @@ pe_status fast_walk(const float* abc, int T, int restart, float eps, P&& product
 
 // Bounds on its operands in the same order, one per product and update (the
 // next X), from the recursions on scalars sampled over each segment's spectrum
-// [0, u^2]; grew: whether one is past the planes' reach (see planes_fit).
+// [0, u^2], evenly and, below the first even sample, by half powers of two (a
+// schedule that has brought the upper part to 1 still moves the lower one); grew: whether one is past the planes' reach (see planes_fit).
 std::vector<double> fast_bounds(const float* abc, int T, int restart, float eps, bool* grew) {
-  constexpr int kSamples = 256;
+  constexpr int kEven = 256, kSamples = kEven + 64;
   typedef std::vector<double> Vec;
   Vec y(kSamples), val[5], out;
   for (auto& v : val) v.assign(kSamples, 0.0);
@@ -309,7 +310,7 @@ std::vector<double> fast_bounds(const float* abc, int T, int restart, float eps,
   auto product = [&](int, int kind, int fp_, int fq_, int fe1, float c1, int fe2, float c2, float cacc, int fout,
                      float cdiag) {
     if (kind == 0)
-      for (int i = 0; i < kSamples; ++i) y[i] = u * u * (i + 1) / kSamples;
+      for (int i = 0; i < kSamples; ++i) y[i] = u * u / kEven * (i < kEven ? i + 1 : std::exp2(-0.5 * (i - kEven + 1)));
     Vec v(kSamples);
     double m = 0.0;
     for (int i = 0; i < kSamples; ++i) {

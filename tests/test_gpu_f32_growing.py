@@ -136,6 +136,37 @@ def test_growing_schedule_fast(pe, shape, k, restart):
     assert e <= 2e-4
 
 
+def _fast_segment_f32(vals, abc):
+    """One segment of the fast iteration in FP32 on the CPU, in the library's form
+    (D = Q - q I, products of rows by rows)."""
+    X = OI.normalise(vals).astype(np.float32)
+    R = X @ X.T
+    D, q = np.zeros_like(R), np.float32(1.0)
+    for a, b, c in np.asarray(abc, dtype=np.float32):
+        B = b * R + c * (R @ R.T)
+        D = a * D + q * B + D @ B.T
+        P = R @ B.T
+        R = a * a * R + 2 * a * P + P @ B.T
+        q = np.float32(q * a)
+    return q * X + D @ X
+
+
+def test_fast_segment_with_a_small_polynomial_at_one(pe):
+    """Four steps for [1/16, 1] leave the upper spectrum within 1e-4 of 1, where the
+    fifth, (1, 10, -10), has B near 0; on the singular values below 1/16, which are
+    still on their way, its B reaches 2.5.  (Segments of five steps cancel by q = 52:
+    no further off than four times the same segment in FP32 on the CPU.)"""
+    import torch
+    abc = np.concatenate([np.asarray(pe.coeffs(1.0 / 16.0, 4).abc).reshape(4, 3), [(1.0, 10.0, -10.0)]])
+    G, v = device_input(synth.usv(synth.rng(9700), 64, 200, np.geomspace(1.0, 1e-3, 64)).G, torch.float32)
+    X = pe.polar(G, T=5, abc=abc, compute="f32", out_dtype=torch.float32, fast_restart=5, fast_eps=0.0)
+    torch.cuda.synchronize()
+    ref = FA.fast_polar_express(v, abc, restart=5, eps=0.0)
+    e, bar = relf(to_np(X), ref), 4.0 * relf(_fast_segment_f32(v, abc), ref)
+    print(f"[grow] small at one relF={e:.3e} bar={bar:.3e}", flush=True)
+    assert e <= bar
+
+
 def test_growing_schedule_plan(pe):
     """Replays of a captured plan, with other work in between."""
     import torch
