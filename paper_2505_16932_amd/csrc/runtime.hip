@@ -662,13 +662,17 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
         d.Xq = (uint8_t*)take(X);
         d.Aq = (uint8_t*)take(A);
       }
-      if (o->fast_restart > 0)
+      if (o->fast_restart > 0) {
         // both D share their fp32 values, which a product replaces in place; a
         // kTiny or kF32M product reads them as operands, and has no planes
         for (int k = 0; k < 5; ++k) {
           d.fb[k] = k == kFbD1 && prec == kF32 ? d.fb[kFbD0] : (float*)take(A * 4);
           d.fbp[k] = prec == kF32 && k != kFbP ? (uint16_t*)take(A * 4) : nullptr;
         }
+        // pe_plan_launch_phase runs the ordinary iteration's phases on any plan
+        d.Af = d.fb[kFbR];
+        d.Bs = d.fb[kFbB];
+      }
       if (o->spectral_init > 0 && !learned) d.vec = (float*)take(((size_t)2 * q.sp + q.Lp) * 4);
       if (learned) {
         int32_t* rec = ws ? (int32_t*)(ws + L->sel_off) + (size_t)i * kSelWords : nullptr;
