@@ -1671,6 +1671,8 @@ hipError_t launch_gemm(int prec, int bt, int kind, const KArgs& all, int grid_ca
     const int rest = a.total > round && a.total % round <= round / 4 ? a.total % round : 0;
     a.total -= rest;
     launch_gemm_t<kBF16, 256>(kind, a, grid_cap, st);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !rest) return e;
     a.tail = a.total;
     a.total = rest;
     return launch_update_tail(a, st);

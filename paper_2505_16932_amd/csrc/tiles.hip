@@ -1024,35 +1024,34 @@ hipError_t launch_small_reduce(int prec, int bt, int kind, const KArgs& a, hipSt
 // round: 0.31 ms per product against 0.18), so those tiles run as quarters of 64
 // in a launch of their own, up to a fourth of a round.
 template <int KIND>
-static void launch_fast_t(int prec, int bt, KArgs a, hipStream_t st) {
+static hipError_t launch_fast_t(int prec, int bt, KArgs a, hipStream_t st) {
   a.tail = -1;
   if (prec == kTiny) {
     typedef SmallTile<64, 4, 1, 0> C;
     hipLaunchKernelGGL((small_fast_kernel<KIND, C>), dim3(a.total < 256 ? a.total : 256), dim3(C::NT), 0, st, a);
-    return;
+    return hipGetLastError();
   }
   typedef SmallTile<64, 4, 1, 2, 64> Q;
   if (bt == kTileTiny) {
     hipLaunchKernelGGL((small_fast_kernel<KIND, Q>), dim3(a.total < 256 ? a.total : 256), dim3(Q::NT), 0, st, a);
-    return;
+    return hipGetLastError();
   }
   typedef SmallTile<128, 1, 1, 2> C;
   constexpr int kRound = 512;
   const int rest = a.total > kRound && a.total % kRound <= kRound / 4 ? a.total % kRound : 0;
   a.total -= rest;
   hipLaunchKernelGGL((small_fast_kernel<KIND, C>), dim3(a.total < kRound ? a.total : kRound), dim3(C::NT), 0, st, a);
-  if (rest) {
-    a.tail = a.total;
-    a.total = 4 * rest;
-    hipLaunchKernelGGL((small_fast_kernel<KIND, Q>), dim3(a.total < 256 ? a.total : 256), dim3(Q::NT), 0, st, a);
-  }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !rest) return e;
+  a.tail = a.total;
+  a.total = 4 * rest;
+  hipLaunchKernelGGL((small_fast_kernel<KIND, Q>), dim3(a.total < 256 ? a.total : 256), dim3(Q::NT), 0, st, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_fast(int prec, int bt, int kind, const KArgs& a, hipStream_t st) {
   if (a.total <= 0) return hipSuccess;
-  if (kind == KIND_GRAM) launch_fast_t<KIND_GRAM>(prec, bt, a, st);
-  else launch_fast_t<KIND_A2>(prec, bt, a, st);
-  return hipGetLastError();
+  return kind == KIND_GRAM ? launch_fast_t<KIND_GRAM>(prec, bt, a, st) : launch_fast_t<KIND_A2>(prec, bt, a, st);
 }
 
 hipError_t launch_planes(const KArgs& a, hipStream_t st) {
