@@ -1039,8 +1039,8 @@ __device__ __forceinline__ void upd_read8(const float* cs, int row, int col, flo
 }
 
 // 8 values of a row of the caller's output (row gr, columns gc..) and the Muon
-// weight step on the same positions (from the bf16 X where X leaves as bf16 or
-// not at all, as it is usually applied)
+// weight step on the same positions (from the bf16 X where X leaves as bf16, so
+// that the two agree)
 __device__ __forceinline__ void upd_result(const KArgs& args, CDesc& d, int gr, int gc, int rows, int cols, const float (&v)[8]) {
   if (gr >= rows || gc >= cols) return;
   const bool whole = gc + 8 <= cols;
@@ -1070,7 +1070,7 @@ __device__ __forceinline__ void upd_result(const KArgs& args, CDesc& d, int gr, 
   }
   if (d.W) {
     const float keep = 1.0f - args.mlr * args.mwd;
-    const bool rounded = !d.Out || d.out_bf16;
+    const bool rounded = d.Out && d.out_bf16;
     const size_t o = (size_t)gr * d.ldw + gc;
     const bool vec = whole && ((uintptr_t)d.W % 16 == 0) && d.ldw % (d.w_bf16 ? 8 : 4) == 0;
     float w[8];

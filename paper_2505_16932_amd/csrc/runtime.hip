@@ -381,7 +381,9 @@ int prec_for(const pe_opts* o, const pe_matrix& m, bool fit) {
 // matrices; the autotuner's batches carry ~3e12 per step) or with more than
 // kBatchTiles update tiles of 256 (four rounds on the 256-CU part), where padding
 // to 256 costs at most 1.35 times the work of padding to 128, or with two rounds,
-// kBatchTilesMin, where it costs at most 1.1 times; "x1" below and otherwise.
+// kBatchTilesMin, where it costs at most 1.1 times (unless a weight step goes with
+// a bf16 output, which the 256 tile takes it from, the small ones from the FP32
+// X_T); "x1" below and otherwise.
 // e4m3 calls, whose small tiles convert while staging, count tiles and FLOP only.
 // Measured per call, 256 against 128: 1536 x 1536 x 16 (576 tiles) 1.61 and 2.07
 // ms, 1024 x 4096 x 8 (512) 0.94 and 1.04, 2048 x 2048 x 8 (512) 1.79 and 1.90,
@@ -462,6 +464,7 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
   // update tiles of the whole call at the 256 tile (the built-in tile rule)
   int64_t upd256 = 0;
   double call_flops = 0.0, work256 = 0.0, work128 = 0.0;
+  bool step_bf16 = false;
   for (int i = 0; i < count; ++i) {
     const pe_matrix& m = mats[i];
     if (m.m <= 0 || m.n <= 0) continue;
@@ -469,6 +472,7 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
     upd256 += round_up(s, kTileLarge) / kTileLarge * (round_up(Lx, kTileLarge) / kTileLarge);
     call_flops += 3.0 * (double)s * s * Lx + (double)s * s * s;
     auto work = [&](int t) { return (double)round_up(s, t) * round_up(s, t) * round_up(Lx, t); };
+    step_bf16 = step_bf16 || (m.W && m.X && m.x_dtype == PE_BF16);
     if (s > 256) {  // (smaller ones take the small tiles in either regime)
       work256 += work(kTileLarge);
       work128 += work(kTileSmall);
@@ -477,7 +481,7 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
   const bool fp8 = o->compute == PE_COMPUTE_FP8 && o->fp8_steps > 0;
   const bool large = call_flops >= kBatchFlops || upd256 > kBatchTiles;
   const bool batch_regime = fp8 ? large : (large && work256 <= 1.35 * work128) ||
-                                          (upd256 >= kBatchTilesMin && work256 <= 1.1 * work128);
+                                          (upd256 >= kBatchTilesMin && work256 <= 1.1 * work128 && !step_bf16);
   // first pass: precision and tile; the second needs the call's totals
   struct Shape { int64_t s, L, sp, Lp; int nb, nbL, nbs, syrk, upd, prep, prec, bt, sbt, cls, scls; bool family, res; };
   std::vector<Shape> sh;

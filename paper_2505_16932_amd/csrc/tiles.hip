@@ -556,8 +556,9 @@ __device__ __forceinline__ void small_epi_syrk(const KArgs& args, CDesc& d, int 
 }
 
 // 16 values of a row of the caller's output (row gr, columns gc..) and the Muon
-// weight step W <- (1 - lr wd) W - lr X_T on the same positions; 16-byte
-// accesses where the row allows them
+// weight step W <- (1 - lr wd) W - lr X_T on the same positions (the last tiles of
+// a 256-tile update: from the bf16 X where X leaves as bf16, like its other tiles);
+// 16-byte accesses where the row allows them
 __device__ __forceinline__ void store_result(const KArgs& args, CDesc& d, int gr, int gc, int rows, int cols,
                                              const float (&v)[16]) {
   if (gr >= rows || gc >= cols) return;
@@ -582,6 +583,7 @@ __device__ __forceinline__ void store_result(const KArgs& args, CDesc& d, int gr
   }
   if (d.W) {
     const float keep = 1.0f - args.mlr * args.mwd;
+    const bool rounded = args.tail >= 0 && d.Out && d.out_bf16;
     const size_t o = (size_t)gr * d.ldw + gc;
     const bool vec = whole && ((uintptr_t)d.W % 16 == 0) && d.ldw % (d.w_bf16 ? 8 : 4) == 0;
     float w[16];
@@ -596,7 +598,7 @@ __device__ __forceinline__ void store_result(const KArgs& args, CDesc& d, int gr
       }
     }
 #pragma unroll
-    for (int e = 0; e < 16; ++e) w[e] = __builtin_fmaf(-args.mlr, v[e], keep * w[e]);
+    for (int e = 0; e < 16; ++e) w[e] = __builtin_fmaf(-args.mlr, rounded ? bf2f(f2bf(v[e])) : v[e], keep * w[e]);
     if (vec) {
       if (d.w_bf16) store16((uint16_t*)d.W + o, w);
       else store16((float*)d.W + o, w);
