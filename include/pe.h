@@ -174,9 +174,12 @@ typedef struct {
    * k-stages per part, A^2 at least 16), summed in split order by a
    * reduction kernel that runs the epilogue (deterministic).  0 = library
    * choice (up to 64), 1 = never split, n in 2..64 = at most n.  The
-   * automatic factor depends on the whole call, so a matrix's result agrees
-   * across calls and settings up to the FP32 summation order; with split_k = 1
-   * it is the same bits in any call that runs it on the same tiles.  PE_EINVAL outside 0..64. */
+   * automatic factor, the tiles and other choices that order sums depend on
+   * the whole call, so a matrix's result agrees across calls and settings up
+   * to the FP32 summation order; with split_k = 1 they depend on the matrix
+   * alone, and it is the same bits in any call with the same opts.tile of 1 or
+   * 2 (with 0, in any call whose regime gives it the same tile id, see
+   * pe_tile_table_load).  PE_EINVAL outside 0..64. */
   int32_t split_k;
   /* Fast rectangular iteration (Appendix G, Algorithm 4): with fast_restart =
    * k >= 1 the T steps run in segments of k steps, each computing the

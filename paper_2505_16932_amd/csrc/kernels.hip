@@ -1668,7 +1668,7 @@ hipError_t launch_gemm(int prec, int bt, int kind, const KArgs& all, int grid_ca
   KArgs a = all;
   if (kind == KIND_UPD) {
     const int round = grid_for(1 << 30, grid_cap, gemm_kernel<kBF16, KIND_UPD, 256>, WaveCfg<kBF16, 256>::NT);
-    const int rest = a.total > round && a.total % round <= round / 4 ? a.total % round : 0;
+    const int rest = !a.alike && a.total > round && a.total % round <= round / 4 ? a.total % round : 0;
     a.total -= rest;
     launch_gemm_t<kBF16, 256>(kind, a, grid_cap, st);
     const hipError_t e = hipGetLastError();

@@ -136,6 +136,7 @@ struct KArgs {
   int32_t tmax;          // rows of the selectable coefficient table
   int32_t prep_group;    // 64 x 64 tiles per norm-pass item
   int32_t fold_norm;     // no finalize launch: readers of sigma add up the partial sums
+  int32_t alike;         // split_k = 1: nothing that orders sums depends on the launch's size
   float a, b, c;         // coefficients of step t (fixed schedule)
   const float* sel_coef; // [n_sched][tmax][3] or nullptr: per-matrix class schedules
   int32_t raw_a2;        // step-1 A^2 of the learned path: store A^2 and its moments

@@ -128,6 +128,7 @@ struct Layout {
   size_t sel_off = 0;  // learned plans: kSelWords words per matrix (class, flag, features, estimate)
   int prep_group = kPrepGroup;
   bool fold_norm = false; // KArgs::fold_norm
+  bool alike = false;     // KArgs::alike
   // item tables in use, packed behind the descriptors: word offset of each
   // phase and class, and of each class's Gram order (-1: none)
   int32_t tab[PH_N][kNCls], tab_ord[kNCls];
@@ -439,6 +440,12 @@ void small_tiles(int prec, int64_t s, int64_t L, int64_t tiles128, int* ubt, int
   *sbt = *ubt == kTileTiny || (s <= 1536 && !full) ? kTileTiny : kTileSmall;
 }
 
+// With split_k = 1 a matrix has the same bits in every call that gives it the same
+// tile id: whatever orders its sums (64 or 128 tiles, the resident kernel, the
+// norm's items, the ring's k groups, smaller tiles in a short last round) then
+// depends on the matrix alone.
+bool alike(const pe_opts* o) { return o->split_k == 1; }
+
 // A matrix that the resident kernel can run: bf16 products in the plain
 // iteration (no e4m3 step, learned choice or spectrum-aware step), at most 64
 // rows and 1024 columns after orientation.
@@ -508,7 +515,7 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
     }
     sh.push_back(q);
   }
-  const bool resident = fits == present || fits >= kResidentMany;
+  const bool resident = fits == present || fits >= kResidentMany || alike(o);
   for (auto& q : sh) {
     q.res = q.res && resident;
     if (q.res) L->resident = true;
@@ -524,17 +531,25 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
   // 2.51 against 2.77 ms per call).  A tile forced by the caller stays as it is.
   auto mixed = [&](const Shape& q) { return q.prec == kBF16 && q.bt == kTileLarge && !fp8; };
   int64_t n128 = 0, n256 = 0;
-  for (const auto& q : sh) {
-    if (!mixed(q) || q.s <= 768) continue;
+  auto fewer_rounds = [&]() { return o->tile == 0 && 1.15 * (2 * ((n128 + 511) / 512)) < 4.0 * ((n256 + 255) / 256); };
+  auto count_tiles = [&](const Shape& q) {
     const int64_t b = (q.s + 255) / 256;
     n256 += b * (b + 1) / 2;
     n128 += b * (2 * b + 1);
-  }
-  const bool syrk128 = o->tile == 0 && 1.15 * (2 * ((n128 + 511) / 512)) < 4.0 * ((n256 + 255) / 256);
+  };
+  for (const auto& q : sh)
+    if (mixed(q) && q.s > 768) count_tiles(q);
+  bool syrk128 = fewer_rounds();
   // second pass: the small family's tiles, padded shapes and tile counts
   for (int i = 0; i < count; ++i) {
     Shape& q = sh[i];
     if (q.s > 0 && !q.res) {
+      if (alike(o)) {  // as in a call of its own
+        tiles128 = (q.s + 127) / 128 * ((q.L + 127) / 128);
+        n128 = n256 = 0;
+        count_tiles(q);
+        syrk128 = fewer_rounds();
+      }
       if (q.family) small_tiles(q.prec, q.s, q.L, tiles128, &q.bt, &q.sbt);
       if (mixed(q) && (q.s <= 768 || syrk128)) q.sbt = kTileSmall;
       const int bt = q.bt;
@@ -561,12 +576,13 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
   // otherwise; FP32 MFMA keeps its four, and with them the bits of its norm.
   // Without the finalize launch (4.8 us) when every matrix runs the small tiles
   // and has few partial sums.
-  L->prep_group = prep_tiles <= 1024 && !f32m ? 1 : kPrepGroup;
+  L->prep_group = prep_tiles <= 1024 && !f32m && !alike(o) ? 1 : kPrepGroup;
   for (auto& q : sh) {
     q.prep = (q.prep + L->prep_group - 1) / L->prep_group;
     most_prep = std::max<int64_t>(most_prep, q.prep);
   }
-  L->fold_norm = small_only && most_prep <= kFoldPartials && !learned_mode(o);
+  L->fold_norm = small_only && most_prep <= kFoldPartials && !learned_mode(o) && !alike(o);
+  L->alike = alike(o);
   int want[kNCls];
   for (int c = 0; c < kNCls; ++c)
     want[c] = syrk_total[c] > 0 ? (int)std::min<int64_t>(64, (kFillTarget + syrk_total[c] - 1) / syrk_total[c]) : 1;
@@ -909,6 +925,7 @@ KArgs base_args(const pe_plan* p) {
   a.norm_mode = p->norm_mode;
   a.prep_group = p->L.prep_group;
   a.fold_norm = p->L.fold_norm;
+  a.alike = p->L.alike;
   a.tail = -1;
   a.tmax = p->T;
   a.mbeta = p->muon_beta;

@@ -946,14 +946,16 @@ __global__ __launch_bounds__(kThreads) void planes_kernel(KArgs args) {
 // one block's loads and epilogue run beside the other's products.  Stages are
 // 64 deep but for the deep ring of the fp32 path's 64 tile, where two stages of
 // 32 fit in the place of one of 64 and a short K feeds twice the waves (64 x 64:
-// 86 us per call against 101, 768 x 768 226 against 239).
+// 86 us per call against 101, 768 x 768 226 against 239).  The deep rings of the
+// 128 tile belong to two groups of waves that share out k, another order of the
+// sums: not where results may not depend on the call (KArgs::alike).
 template <int KIND, typename C>
 static void launch_small_c(const KArgs& a, int cap, hipStream_t st) {
   hipLaunchKernelGGL((small_gemm_kernel<KIND, C>), dim3(a.total < cap ? a.total : cap), dim3(C::NT), 0, st, a);
 }
 template <int KIND>
 static void launch_small_k(int prec, int bt, const KArgs& a, hipStream_t st) {
-  const bool deep = a.total <= 256;
+  const bool deep = a.total <= 256 && (bt == kTileTiny || !a.alike);
   if (prec == kTiny) {
     if constexpr (KIND != KIND_UPD0 && KIND != KIND_UPDI) launch_small_c<KIND, SmallTile<64, 4, 1, 0>>(a, 256, st);
   } else if (prec == kF32) {
@@ -1040,7 +1042,7 @@ static hipError_t launch_fast_t(int prec, int bt, KArgs a, hipStream_t st) {
   }
   typedef SmallTile<128, 1, 1, 2> C;
   constexpr int kRound = 512;
-  const int rest = a.total > kRound && a.total % kRound <= kRound / 4 ? a.total % kRound : 0;
+  const int rest = !a.alike && a.total > kRound && a.total % kRound <= kRound / 4 ? a.total % kRound : 0;
   a.total -= rest;
   hipLaunchKernelGGL((small_fast_kernel<KIND, C>), dim3(a.total < kRound ? a.total : kRound), dim3(C::NT), 0, st, a);
   const hipError_t e = hipGetLastError();
