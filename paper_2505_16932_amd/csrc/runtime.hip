@@ -1453,8 +1453,8 @@ int32_t pe_tile_count(void) { return 3; }
 const char* pe_tile_name(int32_t tile_id) {
   switch (tile_id) {
     case 0: return "auto";
-    case 1: return "bt128_w2x2_mfma16";
-    case 2: return "bt256_w2x2_mfma32";
+    case 1: return "bt64_bt128_mfma16";
+    case 2: return "bt256_w2x4_mfma32";
   }
   return nullptr;
 }
