@@ -684,11 +684,14 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
       }
       if (o->fast_restart > 0) {
         // both D share their fp32 values, which a product replaces in place; a
-        // kTiny or kF32M product reads them as operands, and has no planes
+        // kTiny or kF32M product reads them as operands, and has no planes (kF32M
+        // still takes their room, one of them for the second D: which of the two
+        // a matrix runs depends on the schedule, its workspace does not)
         for (int k = 0; k < 5; ++k) {
-          d.fb[k] = k == kFbD1 && prec == kF32 ? d.fb[kFbD0] : (float*)take(A * 4);
-          d.fbp[k] = prec == kF32 && k != kFbP ? (uint16_t*)take(A * 4) : nullptr;
+          d.fb[k] = k == kFbD1 && prec != kTiny ? d.fb[kFbD0] : (float*)take(A * 4);
+          d.fbp[k] = prec != kTiny && k != kFbP ? (uint16_t*)take(A * 4) : nullptr;
         }
+        if (prec == kF32M) d.fb[kFbD1] = (float*)d.fbp[kFbD1];
         // pe_plan_launch_phase runs the ordinary iteration's phases on any plan
         d.Af = d.fb[kFbR];
         d.Bs = d.fb[kFbB];
