@@ -711,11 +711,11 @@ pe_status build_layout(int count, const pe_matrix* mats, const pe_opts* o, char*
     // Callers size and share workspaces by shape and compute type alone, and the
     // static scratch admits matrices by this size: whatever tile or kernel a
     // matrix gets, it is at least an FP32 iterate with two operand copies and A
-    // and B, padded to the 128 (or its 256) tile.
+    // and B (fast iteration: eight s x s matrices), padded to the 128 (or its 256) tile.
     if (q.s > 0) {
       const int pad = std::max(bt, (int)kTileSmall);
       const size_t S = round_up(q.s, pad), XX = S * round_up(q.L, pad), per = o->compute == PE_COMPUTE_F32 ? 4 : 2;
-      off = std::max(off, begin + align_up(XX * (4 + 2 * per) + S * S * 2 * per));
+      off = std::max(off, begin + align_up(XX * (4 + 2 * per) + S * S * (o->fast_restart > 0 ? 32 : 2 * per)));
     }
     L->descs.push_back(d);
     // this matrix's items in its class's tables, none in the others
