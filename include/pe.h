@@ -53,7 +53,9 @@ typedef enum { PE_F32 = 0, PE_BF16 = 1 } pe_dtype;
 /* Arithmetic of the online stage.
  *  PE_COMPUTE_F32 : FP32 iterate; each product takes its FP32 operands as two
  *                   fp16 planes (22 bits, scaled) on fp16 MFMA with FP32
- *                   accumulation, which is no less accurate than FP32 MFMA
+ *                   accumulation; the error of the whole result is at or
+ *                   below FP32 MFMA's on inputs that average rounding out, and
+ *                   rows 1e-8 of the largest keep three to four digits
  *                   (matrices with min(m, n) < 16: FP32 operands, FP64 sums;
  *                   FP32 results of T = 6 with min(m, n) > 1024 or T > 6 with
  *                   min(m, n) > 384, and schedules that grow on [0, 1] past a
@@ -273,7 +275,8 @@ pe_status pe_plan_destroy(pe_plan* plan);
  * reads whatever the plan's buffers hold (run pe_plan_launch first); the
  * buffers are left in an unspecified state, the caller's X untouched unless
  * step = T-1 and phase = 3.  PE_EINVAL for a bad step or phase;
- * PE_EUNSUPPORTED for a plan with the learned choice of l.  Matrices that one
+ * PE_EUNSUPPORTED for a plan with the learned choice of l.  Plans of the fast
+ * rectangular iteration run the ordinary iteration's phases.  Matrices that one
  * kernel runs from norm to output (bf16, min(m, n) <= 64, max(m, n) <= 1024)
  * have no phases: step T-1, phase 3 runs them whole. */
 pe_status pe_plan_launch_phase(pe_plan* plan, int32_t step, int32_t phase, void* stream);

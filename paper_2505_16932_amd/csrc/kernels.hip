@@ -3,8 +3,8 @@
 // A = X X^T, B = b A + c A^2, X = a X + B X).
 //
 // The norm pass, the bf16 and e4m3 products on the 256 tile, the e4m3 products
-// of small matrices and the power method; the 64 and 128 tiles are in tiles.hip,
-// FP32 MFMA in f32.hip, matrices of at most 64 rows in resident.hip.  Each kernel
+// of small matrices, the power method and the init step's B; the 64 and 128 tiles
+// are in tiles.hip, FP32 MFMA in f32.hip, matrices of at most 64 rows in resident.hip.  Each kernel
 // is launched once per phase over the items of every matrix of a call ("grouped"
 // launches; a single matrix is a group of one) and walks its items in a
 // grid-stride loop:
